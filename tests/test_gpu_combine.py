@@ -71,3 +71,37 @@ def test_bad_page_in_a_many_piece_sequence_gives_nan_rows(shape):
     assert (run.out[2].float() == 0).all() and (run.lse[2] == -float("inf")).all()
     qn, qr = w.queries()
     check_sequence(run, 1, reference(w, 1, qn, qr), label=f"combine-badpage-{shape}")
+
+
+# Each way launch_combine spreads a row over waves: (H, B, parts).  Plain rows (R = 16): G = 1, 2, 4, 8 from the
+# mean pieces of a sequence and the row count (17 rows: a last workgroup that is not full); tile order (R = 72, whose
+# last 32-row tile is part padding): one chunk pair per workgroup (four-wave merge), half tiles and whole tiles.
+SPREADS = {
+    "rows-g1-few-pieces": (17, 3, 8), "rows-g2": (17, 5, 40), "rows-g4": (17, 3, 60), "rows-g8": (17, 3, 200), "rows-g4-chunk": (36, 9, 640),
+    "rows-g4-many-rows": (36, 16, 640), "rows-g1-many-rows": (36, 30, 640),
+    "tiles-g4": (72, 5, 90), "tiles-half": (72, 16, 70), "tiles-whole": (72, 60, 150),
+}
+
+
+@pytest.mark.parametrize("spread", list(SPREADS))
+def test_merge_shapes_equal_one_piece_per_sequence(spread):
+    """The merge of many pieces against the same decode with every sequence in one piece, for every launch shape.  Per
+    64-token block both compute the same codes, so the two differ by float32 sums in another order: within 2^-16 of a
+    row's largest output (some 200 terms of at most that size, 2^-24 each), LSE within 2^-18."""
+    H, B, parts = SPREADS[spread]
+    lens = [(5000, 0, 64 * 37 + 5, 1, 700)[i % 5] for i in range(B)]
+    w = wl.custom(B=B, H=H, q_len=1, seq_lens=lens, seed=83, n_new=0)
+    one = runner(w, unsplit=True)
+    run = runner(w, num_splits=parts, cache=(one.kv_latent, one.kv_scale, one.k_rope))
+    for r in (one, run):
+        r.out.fill_(12345.0)
+        r.lse.fill_(12345.0)
+        r.step()
+    torch.cuda.synchronize()
+    a, b = run.out.double().reshape(-1, 512), one.out.double().reshape(-1, 512)
+    assert torch.isfinite(b).all() and not (b == 12345.0).any()
+    assert ((a - b).abs().amax(1) <= 2.0 ** -16 * b.abs().amax(1)).all()
+    la, lb = run.lse.double().reshape(-1), one.lse.double().reshape(-1)
+    fin = torch.isfinite(lb)
+    assert torch.equal(torch.isfinite(la), fin) and (la[~fin] == lb[~fin]).all()
+    assert ((la - lb)[fin].abs() <= 2.0 ** -18 * lb[fin].abs().clamp_min(1)).all()
