@@ -6,16 +6,11 @@
 // When the decode was given the output (ctrl[0] == 1) it has written the rows of
 // every sequence that at most one piece covers; those are left as they are.
 //
-// Two kernels, one per slot layout (part_tile_offset), each in a few shapes that spread
-// a row over more waves when there are few rows (launch_combine):
-// - one row group (plain rows): G waves per row; lane l owns output dimensions
-//   8l..8l+7.  The pieces' log-sum-exps are read lane-parallel, and a piece whose
-//   weight underflows to zero is not read at all (the row's partial sits in its own
-//   cache lines).
-// - several row groups (tile order): one wave per 32-row x 32-dimension tile or per
-//   chunk pair of it, lane n + 32h on row n of the tile, dimensions 8q + 4h .. +3; every
-//   partial load of a wave reads 1 KiB of consecutive bytes.  Each lane merges its row
-//   with a running maximum, J pieces per round so that their loads overlap.
+// The partials are in accumulator tile order (part_tile_offset): one wave per 32-row x
+// 32-dimension tile or per half or quarter of it, lane n + 32h on row n of the tile,
+// dimensions 8q + 4h .. +3; every partial load of a wave reads 1 KiB of consecutive
+// bytes.  Each lane merges its row with a running maximum, J pieces per round so that
+// their loads overlap.
 
 #include "piece_end.h"
 #include "snapmla_device.h"
@@ -61,143 +56,14 @@ __device__ Pieces pieces_of(const CombineArgs& a, int b) {
   return P;
 }
 
-// The bf16 or float32 results of 8 consecutive output dimensions (elements 8i .. 8i+7 of a row).
-__device__ __forceinline__ void store_row8(const CombineArgs& a, int64_t orow, int i, const float (&o)[8]) {
-  if (a.out_dtype == 1) {
-    v4f* dst = reinterpret_cast<v4f*>(reinterpret_cast<float*>(a.out) + orow * kDc + 8 * i);
-    dst[0] = v4f{o[0], o[1], o[2], o[3]};
-    dst[1] = v4f{o[4], o[5], o[6], o[7]};
-  } else {
-    uint4 pk;
-    pk.x = f32_to_bf16_bits(o[0]) | (f32_to_bf16_bits(o[1]) << 16);
-    pk.y = f32_to_bf16_bits(o[2]) | (f32_to_bf16_bits(o[3]) << 16);
-    pk.z = f32_to_bf16_bits(o[4]) | (f32_to_bf16_bits(o[5]) << 16);
-    pk.w = f32_to_bf16_bits(o[6]) | (f32_to_bf16_bits(o[7]) << 16);
-    reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(a.out) + orow * kDc)[i] = pk;
-  }
-}
-
-// G waves per row (G <= 4: a workgroup holds 4 / G rows; above: one row): wave g of a
-// row takes the pieces g, g + G, ... and the waves' weighted sums meet in LDS.
-template <int G>
-__global__ __launch_bounds__(G <= 4 ? 256 : 64 * G) void combine_rows_kernel(CombineArgs a) {
-  constexpr int kRows = G <= 4 ? 4 / G : 1;           // rows of a workgroup
-  constexpr int kFly = 4;                             // partial rows in flight per wave
-  const int lane = threadIdx.x & 63;
-  const int w = threadIdx.x >> 6;
-  const int g = w % G, wr = w / G;
-  const int64_t wv = (int64_t)blockIdx.x * kRows + wr;
-  const bool live = wv < (int64_t)a.B * a.R;          // (kRows == 1: always)
-  if (G == 1 && !live) return;
-  const int b = live ? (int)(wv / a.R) : 0, r = live ? (int)(wv % a.R) : 0;
-
-  const Pieces P = pieces_of(a, b);
-  const int first = P.first, last = P.last;
-  const bool work = live && !(a.ctrl[0] == 1 && last <= first);
-  if (G == 1 && !work) return;
-  auto exists = [&](int i) { return P.exists(i); };
-  auto pid = [&](int i) { return P.pid(i); };
-
-  // pass 1: lane i reads the log-sum-exp of candidate piece first + i (64 at a
-  // time), the wave reduces the maximum and NaN flag; the first 64 stay in x0 for
-  // pass 2 (every wave of a row reads them all)
-  float M = -INFINITY;
-  bool anynan = false;
-  float x0 = -INFINITY;
-  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  float S = 0.0f;
-  if (work) {
-    for (int i0 = first; i0 <= last; i0 += 64) {
-      const int i = i0 + lane;
-      float x = -INFINITY;
-      if (i <= last && exists(i)) x = a.part_lse[pid(i) * a.rows_pad + r];
-      if (i0 == first) x0 = x;
-      anynan |= x != x;
-      M = fmaxf(M, x);
-    }
-    M = wave_max(M);
-    anynan = __builtin_amdgcn_ballot_w64(anynan) != 0;
-    // pass 2: weights exp(LSE_i - M) (lane-parallel), then this wave's weighted rows,
-    // kFly pieces per round so that their loads overlap
-    if (M > -INFINITY && !anynan) {
-      for (int i0 = first; i0 <= last; i0 += 64) {
-        const int i = i0 + lane;
-        float wi = 0.0f;
-        if (i <= last && exists(i)) {
-          const float x = i0 == first ? x0 : a.part_lse[pid(i) * a.rows_pad + r];
-          wi = x > -INFINITY ? expf(x - M) : 0.0f;
-        }
-        S += wi;
-        const int cnt = min(64, last - i0 + 1);
-        for (int j = g; j < cnt; j += kFly * G) {
-          v4f u[kFly][2];
-          float wj[kFly];
-#pragma unroll
-          for (int t = 0; t < kFly; ++t) {
-            const int jt = j + t * G;
-            wj[t] = jt < cnt ? __shfl(wi, jt & 63, 64) : 0.0f;   // zero for missing / empty pieces
-            const bool use = wj[t] != 0.0f;
-            const int ij = min(i0 + jt, last);       // in range even when unused
-            const v4f* src = reinterpret_cast<const v4f*>(a.part_o + (pid(ij) * a.rows_pad + r) * kDc + 8 * lane);
-            u[t][0] = use ? src[0] : v4f{0.f, 0.f, 0.f, 0.f};
-            u[t][1] = use ? src[1] : v4f{0.f, 0.f, 0.f, 0.f};
-          }
-#pragma unroll
-          for (int t = 0; t < kFly; ++t) {
-            acc[0] += wj[t] * u[t][0][0]; acc[1] += wj[t] * u[t][0][1];
-            acc[2] += wj[t] * u[t][0][2]; acc[3] += wj[t] * u[t][0][3];
-            acc[4] += wj[t] * u[t][1][0]; acc[5] += wj[t] * u[t][1][1];
-            acc[6] += wj[t] * u[t][1][2]; acc[7] += wj[t] * u[t][1][3];
-          }
-        }
-      }
-      // wave sum of the weights
-      for (int o = 32; o > 0; o >>= 1) S += __shfl_xor(S, o, 64);
-    }
-  }
-  if constexpr (G > 1) {
-    __shared__ v4f sums[kRows][G][kDc / 4];
-    sums[wr][g][2 * lane] = v4f{acc[0], acc[1], acc[2], acc[3]};
-    sums[wr][g][2 * lane + 1] = v4f{acc[4], acc[5], acc[6], acc[7]};
-    __syncthreads();
-    if (!work || g != 0) return;
-    for (int o = 1; o < G; ++o) {
-      const v4f p = sums[wr][o][2 * lane], q = sums[wr][o][2 * lane + 1];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        acc[j] += p[j];
-        acc[4 + j] += q[j];
-      }
-    }
-  }
-  const bool bad = a.flags[b] != 0 || anynan;
-  float o[8];
-  float lse;
-  if (bad) {
-    const float nanv = __builtin_nanf("");
-    for (int j = 0; j < 8; ++j) o[j] = nanv;
-    lse = nanv;
-  } else if (!(M > -INFINITY)) {
-    for (int j = 0; j < 8; ++j) o[j] = 0.0f;
-    lse = -INFINITY;
-  } else {
-    const float inv = 1.0f / S;
-    for (int j = 0; j < 8; ++j) o[j] = acc[j] * inv;
-    lse = M + logf(S);
-  }
-  const int64_t orow = (int64_t)b * a.R + r;
-  store_row8(a, orow, lane, o);
-  if (a.lse != nullptr && lane == 0) a.lse[orow] = lse;
-}
-
 // A wave merges Q of the four chunk pairs (8 dimensions each) of a 32 x 32 tile, J
-// pieces per round; with G > 1 the four waves of a workgroup share one such part and
+// pieces per round; with G > 1 the G waves of a workgroup share one such part and
 // wave g takes the pieces g, g + G, ...
 template <int Q, int G, int J>
-__global__ __launch_bounds__(256) void combine_tiles_kernel(CombineArgs a) {
-  static_assert(G == 1 || G == 4, "waves of a part");
+__global__ __launch_bounds__(G <= 4 ? 256 : 64 * G) void combine_kernel(CombineArgs a) {
+  static_assert(G == 1 || G >= 4, "waves of a part");
   constexpr int kParts = 16 / Q;                     // parts of a (sequence, row tile, dimension quarter)
-  constexpr int kPerWg = 4 / G;                      // parts of a workgroup
+  constexpr int kPerWg = G == 1 ? 4 : 1;             // parts of a workgroup
   const int lane = threadIdx.x & 63;
   const int n = lane & 31, h = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -323,47 +189,32 @@ __global__ __launch_bounds__(256) void combine_tiles_kernel(CombineArgs a) {
   if (a.lse != nullptr && dq == 0 && T == 0 && q0 == 0 && h == 0) a.lse[orow] = lse;
 }
 
-template <int G>
-static hipError_t launch_rows(const CombineArgs& a, hipStream_t stream) {
-  constexpr int kRows = G <= 4 ? 4 / G : 1;
-  const int64_t blocks = ((int64_t)a.B * a.R + kRows - 1) / kRows;
-  if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(combine_rows_kernel<G>, dim3((unsigned)blocks), dim3(G <= 4 ? 256 : 64 * G), 0, stream, a);
-  return hipGetLastError();
-}
-
 template <int Q, int G, int J>
-static hipError_t launch_tiles(const CombineArgs& a, hipStream_t stream) {
-  const int64_t blocks = (int64_t)a.B * ((a.R + 31) / 32) * 4 * (4 * G / Q);
+static hipError_t launch_shape(const CombineArgs& a, hipStream_t stream) {
+  const int64_t blocks = (int64_t)a.B * ((a.R + 31) / 32) * 4 * (16 / Q) / (G == 1 ? 4 : 1);
   if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((combine_tiles_kernel<Q, G, J>), dim3((unsigned)blocks), dim3(256), 0, stream, a);
+  hipLaunchKernelGGL((combine_kernel<Q, G, J>), dim3((unsigned)blocks), dim3(G <= 4 ? 256 : 64 * G), 0, stream, a);
   return hipGetLastError();
 }
 
 // How a row is spread over waves.  A merge of few rows is bound by the chain of loads of
 // one wave (a memory round trip per round of pieces) and leaves the chip idle; a merge of
 // many rows is bound by the partials' bytes, and there the LDS exchange and the smaller
-// parts only cost.  Measured, us per call back to back (about 8 of them the host's launch):
-//   plain rows  192 rows x 86 pieces: G = 1 19.3, 4 9.8, 8 8.5;  64 x 257: 39.0, 17.2, 12.7 (16: 15.0);
-//               1024 x 17: G = 1 10.0, 4 8.2, 8 9.1;  2048 x 9: G = 1 9.2, 2 9.8, 4 11.1;  4096 x 5: 10.8, 13.8, 15.3
-//   tile order  512 rows x 33 pieces: <4,1,4> 21.7, <1,1,8> 13.5, <1,4,8> 8.5;  256 x 65: 34.4, 20.9, 8.7;
-//               32768 x 1.5: <4,1,4> 25.5, <2,1,8> 33.4, <1,4,8> 109.8
-//   (in a graph, without the launch) 1024 x 6: <4,1,4> 6.1, <2,1,4> 5.3, <1,4,8> 9.5;  1536 x 9: 8.5, 7.4, 11.5;
-//               768 x 17: 11.9, 9.2, 7.8
+// parts only cost.  Measured, us per call in a graph (rows x mean pieces; shapes <Q, G, J>):
+//   64 x 257  <4,1,4> 85  <2,4,4> 20.0  <1,4,8> 15.8   192 x 86  38  10.6  9.4
+//   512 x 33  21.7  8.5  8.4     256 x 17  13.0  6.5  6.8     1024 x 17  16.6  8.0  10.2
+//   1024 x 9  8.7  6.1  9.1      512 x 9  8.5  6.1  8.9      512 x 32  14.1  6.6  6.8
+//   2048 x 9  <4,1,4> 11.7  <2,1,4> 10.0  <2,4,4> 9.6        4096 x 5  11.1  10.9  13.6
+//   32768 x 1.5  <4,1,4> 24.6  <2,1,4> 25.2  <2,4,4> 56
 hipError_t launch_combine(const CombineArgs& a, hipStream_t stream) {
   const int64_t rows = (int64_t)a.B * a.R;
   if (rows <= 0) return hipSuccess;
   // pieces of an average sequence (fixed chunks: of the longest)
   const int mean = a.chunk_blocks == 0 ? a.num_splits / a.B + 1 : a.num_splits;
-  if (a.rows_pad > 64) {
-    if (rows <= 1024 && mean >= 16) return launch_tiles<1, 4, 8>(a, stream);
-    if (rows <= 4096) return launch_tiles<2, 1, 4>(a, stream);
-    return launch_tiles<4, 1, 4>(a, stream);
-  }
-  if (rows > 1024 || mean < 8) return launch_rows<1>(a, stream);
-  if (mean < 16) return launch_rows<2>(a, stream);
-  if (mean < 32 || rows > 256) return launch_rows<4>(a, stream);
-  return launch_rows<8>(a, stream);
+  if (rows <= 256 && mean >= 64) return launch_shape<1, 8, 8>(a, stream);
+  if (rows <= 1024 || (rows <= 2048 && mean >= 8)) return launch_shape<2, 4, 4>(a, stream);
+  if (rows <= 4096) return launch_shape<2, 1, 4>(a, stream);
+  return launch_shape<4, 1, 4>(a, stream);
 }
 
 }  // namespace snapmla

@@ -64,6 +64,7 @@
 // stale bytes; their logits are masked to -inf, their fused probabilities
 // forced to 0 and their V bytes cleared before the PV product.
 
+#include "decode_sync.h"
 #include "piece_end.h"
 #include "snapmla_device.h"
 #include "snapmla_internal.h"
@@ -88,15 +89,7 @@ constexpr int kXpBytes = 4 * 4 * 4;             // page-id ring of the PV waves 
 constexpr int kXpBase = kXBase + kXcBytes + kXgBytes + kXfBytes;
 constexpr int kSmemBytes = kXpBase + kXpBytes;
 static_assert(kSmemBytes <= 160 * 1024, "LDS budget of one workgroup");
-constexpr float kLn2 = 0.69314718055994531f;
 static_assert(20 + kPieceStores < 64, "wait counter range");
-
-// Branch weights for the block layout: the rare cases of a period (a piece start
-// or end, a sequence's last page, the first and last periods) are laid out off the
-// straight path, which then runs with fewer taken branches.
-// (macros: the hint must sit in the branch condition itself to reach the layout)
-#define likely(c) __builtin_expect(!!(c), 1)
-#define unlikely(c) __builtin_expect(!!(c), 0)
 
 // Latent rows are stored with 16-byte chunk c of token t at chunk c ^ swz(t),
 // RoPE rows with chunk c at c ^ rswz(t).  Sixteen consecutive tokens (the QK
@@ -106,43 +99,10 @@ static_assert(20 + kPieceStores < 64, "wait counter range");
 __device__ __forceinline__ int swz(int t) { return (t & 15) ^ (((t >> 4) & 1) << 2); }
 __device__ __forceinline__ int rswz(int t) { return (t >> 1) & 7; }
 
-// Per-row results at a piece end from the published state {gamma, l, m, sigma_P} of
-// the row's last block: 1/l and LSE = ln 2 (m + log2(sigma_P l)) (m in log2 units;
-// Algorithm 1 finalisation); 0 and -inf for a row without tokens, NaN for a bad piece.
 __device__ __forceinline__ void piece_row_results(v4f gl0, v4f gl1, bool bad, float (&inv)[2], float (&lse)[2]) {
-#pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const v4f gl = r == 0 ? gl0 : gl1;
-    const float lfin = gl[1];
-    const bool empty = !(lfin > 0.0f);
-    inv[r] = empty ? 0.0f : 1.0f / lfin;
-    lse[r] = empty ? -INFINITY : (gl[2] + log2f(gl[3] * lfin)) * kLn2;
-    if (bad) {
-      inv[r] = __builtin_nanf("");
-      lse[r] = __builtin_nanf("");
-    }
-  }
+  piece_row_result(gl0, bad, inv[0], lse[0]);
+  piece_row_result(gl1, bad, inv[1], lse[1]);
 }
-
-// Handshake flags in LDS.  A wave's LDS operations complete in issue order, so
-// a flag stored after lds_wait_all() is seen only after the data stored before it.
-// (the builtin rather than inline asm: the compiler's own wait-count pass then
-// knows that every LDS result is in, and inserts no later waits for them)
-__device__ __forceinline__ void lds_wait_all() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0); vmcnt and expcnt left alone
-  asm volatile("" ::: "memory");
-}
-__device__ __forceinline__ void flag_store(int* f, int v) {
-  __hip_atomic_store(f, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-__device__ __forceinline__ int flag_load(const int* f) {
-  return __hip_atomic_load(const_cast<int*>(f), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-// Four consecutive flags with one LDS read (an explicit LDS pointer: a generic one
-// would become a flat load, which queues behind the page copies).
-typedef __attribute__((address_space(3))) volatile v4i lds_flags4;
-__device__ __forceinline__ v4i flag_load4(const int* f) { return *(const lds_flags4*)(f); }
 // all four QK waves have published block k
 __device__ __forceinline__ bool flags_past(v4i f4, int k) { return f4[0] > k && f4[1] > k && f4[2] > k && f4[3] > k; }
 
@@ -817,6 +777,7 @@ __global__ __launch_bounds__(512, 1) void decode_kernel(DecodeArgs a, const int3
 }
 
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream) {
+  if (!a.qk_exact) return launch_decode_stagger(a, stream);
   const int units = a.chunk_blocks == 0 ? a.num_splits : a.B * a.num_splits;
   if (units <= 0) return hipSuccess;
   const int64_t grid = (int64_t)((units + 7) / 8) * 8 * a.G;

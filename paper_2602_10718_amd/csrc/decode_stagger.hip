@@ -1,0 +1,572 @@
+// FP8 MLA decode kernel (Algorithm 1; Appendix D recurrences; Section 3.2) with the
+// QK waves of even and odd blocks staggered by one period.
+//
+// One workgroup = 8 waves (two per SIMD) = 32 RT query rows (RT = 1 or 2) of one row
+// group x a contiguous range of 64-token KV blocks (one page each).
+//   QK waves  w = 0..3: rows 32 (w & 1) .. +31 against the 64 tokens of every second
+//             block (w >> 1: even or odd blocks), 32x32 tiles with the tokens on the
+//             MFMA M axis: one lane holds 32 logits of one row and lane ^ 32 the other
+//             32.  A wave has two periods for a block: operand reads and products in the
+//             first, softmax, scale fusion and E4M3 probability codes in the second.
+//             With RT = 1 the waves w & 1 == 1 only copy pages.
+//   PV waves  w = 4..7, dq = w-4: O^T of all rows for latent dimensions
+//             128dq..128dq+127; they own the output accumulator and write the pieces.
+// One workgroup barrier opens each period j.  In period j, the QK waves of block j's
+// parity form the logits of block j; the others turn block j-1 into codes and row state,
+// publish them in LDS, raise their flags and copy block j+2 into LDS (half a page each; with
+// RT = 1 the copying waves take half a page in every period); the PV waves run the
+// products of block j-2 from registers, take block j-1's V^T tiles into registers, wait for
+// its flags and take its codes and state.  The running maximum, normaliser and block scale
+// of a row pass from one parity's wave to the other's through the published state, a period
+// old when it is read.
+//
+// Why this split: a page is read from LDS by two QK waves instead of four (32 rows per
+// operand byte instead of 16), and no wave has to finish the chain page -> codes -> product
+// within one period, so the period is the longest of three independent stages and the page
+// copies are issued by waves that have time for them.
+//
+// Data movement: each 64-token page (32 KiB E4M3 latent, 8 KiB bf16 RoPE, 256 B scales)
+// is copied HBM -> LDS with 16-byte direct-to-LDS loads two periods before its logits.
+// The latent of block j is read in periods j (QK) and j+1 (PV): a 4-stage ring.  The
+// RoPE/scale part is read in period j only: a 3-stage ring (158 KiB of LDS in all).
+// Latent rows are stored with the 16-byte chunk index XOR-swizzled by the token index
+// (swz) so that both the token-major QK reads and the transposed PV reads avoid bank
+// conflicts.  A workgroup starts from the descriptor of its block range that the prep
+// kernel wrote (range and first sequence): no search of the split plan.
+//
+// Per block (matrices transposed so that one lane owns one query row):
+//   S^T[64 tok x 32 rows]  = K_c^T . q8^T   (32x32x64 FP8 MFMA, K = 512), 2 token tiles
+//                          + K_r^T . q_r^T  (32x32x16 BF16 MFMA, K = 64)
+//   s = log2(e) tau (sigma_q sigma_K acc_c + acc_r)   (Section 3.1 domain alignment,
+//       applied to the two accumulators instead of pre-scaling the RoPE operands)
+//   running max m, block scale sigma_P = max(max(e sigma_K) / 448, 2^-40),
+//   gamma = exp(m_old - m) sigma_p_old / sigma_P, l = gamma l + sum(e) / sigma_P,
+//   codes pi = E4M3(e sigma_K / sigma_P)                 (Appendix D)
+//   O^T[128 dims x rows] = gamma O^T + V^T . P^T          (32x32x64 FP8 MFMA, K = 64 tokens)
+// The FP8 MFMA sums each group of eight consecutive K positions with every product
+// truncated to a multiple of 2^(E-13), E the group's largest exponent sum (the accuracy
+// the parity tests allow for this mode).  V^T is read straight from the token-major
+// latent tile with the LDS transpose read (ds_read_b64_tr_b8; the CDNA counterpart of the
+// paper's V-tile transposition).  The K (token) order of the PV product is the order in
+// which a QK lane holds its 32 codes, so a QK lane's codes are one PV lane's B operand,
+// and the transposed reads fetch V rows in that same order.  Blocks are consumed in
+// increasing order, the monotone order of Appendix E.  Slots past the end of a sequence
+// hold stale bytes; their logits are masked to -inf, their fused probabilities forced to
+// 0 and their V bytes cleared before the PV product.
+
+#include <type_traits>
+
+#include "decode_sync.h"
+#include "piece_end.h"
+#include "snapmla_device.h"
+#include "snapmla_internal.h"
+
+namespace snapmla {
+
+namespace {
+
+constexpr int kLatBytes = kPage * kDc;          // 32768
+constexpr int kRopeBytes = kPage * kDr * 2;     // 8192
+constexpr int kScBytes = kPage * 4;             // 256
+constexpr int kRsBytes = kRopeBytes + kScBytes;  // RoPE + scale part of a page
+constexpr int kLatStages = 4;
+constexpr int kRsStages = 3;
+constexpr int kRsBase = kLatStages * kLatBytes;   // LDS offset of the RoPE/scale ring
+constexpr int kXBase = kRsBase + kRsStages * kRsBytes;
+constexpr int kWaves = 8;
+constexpr int kXcBytes = 64 * 64;               // probability codes [row][64 token slots]; 16-byte
+                                                // chunk c of row r at chunk c ^ ((r >> 2) & 3), so that
+                                                // 16 consecutive rows hit 16 distinct bank groups
+constexpr int kXgBytes = 64 * 16;               // per-row gamma, l, m, sigma_p
+constexpr int kXfBytes = 4 * 4;                 // handshake flags of the QK waves
+constexpr int kXpBytes = 4 * 4 * 4;             // page-id ring of the QK waves [wave][4 slots]
+constexpr int kXpBase = kXBase + kXcBytes + kXgBytes + kXfBytes;
+constexpr int kSmemBytes = kXpBase + kXpBytes;
+static_assert(kSmemBytes <= 160 * 1024, "LDS budget of one workgroup");
+
+// Latent rows are stored with 16-byte chunk c of token t at chunk c ^ swz(t), RoPE rows
+// with chunk c at c ^ rswz(t).  Sixteen consecutive tokens (the QK operand reads) map a
+// given chunk to sixteen distinct 16-byte bank groups, and the eight tokens of one
+// transposed-read group (PV reads: t0..t0+3 and t0+8..t0+11, t0 a multiple of 4) to
+// eight distinct groups of a 128-byte line.
+__device__ __forceinline__ int swz(int t) { return (t & 3) | ((t >> 1) & 4) | ((t << 1) & 8); }
+__device__ __forceinline__ int rswz(int t) { return (t >> 1) & 7; }
+
+template <int RT>
+__global__ __launch_bounds__(512, 1) void decode_stagger_kernel(DecodeArgs a, const int32_t* __restrict__ prefix,
+                                                                const int32_t* __restrict__ page_table,
+                                                                const int32_t* __restrict__ seq_lens) {
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[kSmemBytes];
+  uint8_t* xc = smem + kXBase;                                                 // [64 rows][64] codes
+  float* xg = reinterpret_cast<float*>(smem + kXBase + kXcBytes);               // [64 rows] x 4
+  int* xf = reinterpret_cast<int*>(smem + kXBase + kXcBytes + kXgBytes);        // QK flags
+
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int h = lane >> 5, n = lane & 31;
+
+  // XCD-aware order: the row groups of one unit are 8 apart in launch order, so
+  // they land on the same XCD and share its L2 for the KV pages.
+  const int x8 = blockIdx.x & 7, q8i = blockIdx.x >> 3;
+  const int g = q8i % a.G;
+  const int unit = (q8i / a.G) * 8 + x8;
+  const int units = a.chunk_blocks == 0 ? a.num_splits : a.B * a.num_splits;
+  if (unit >= units) return;
+
+  // ---- the global block range of this workgroup and its first piece, from the
+  // start descriptor the prep kernel wrote (one scalar load, no search) ------
+  const int32_t* dsc = a.desc + (int64_t)unit * kDescInts;
+  const int gstart = dsc[kDescStart], gend = dsc[kDescEnd];
+  if (gstart >= gend) return;
+  const int nblocks = gend - gstart;
+  // piece of the wave's current block (scalar)
+  int cur_b = dsc[kDescSeq], cur_p0 = dsc[kDescP0], cur_end = dsc[kDescP1], cur_n = dsc[kDescLen];
+  // moves on to the piece that holds global block gb >= cur_end (the three loads of the
+  // usual case, the next sequence, are issued together: one memory round trip)
+  auto seek = [&](int gb) {
+    int b = cur_b + 1;
+    int p0 = prefix[b], p1 = prefix[b + 1], nb = seq_lens[b];
+    asm volatile("" ::"s"(nb));                   // keeps the length load beside the prefix loads
+    while (p1 <= gb) {
+      ++b;
+      p0 = p1;
+      p1 = prefix[b + 1];
+      nb = seq_lens[b];
+    }
+    cur_b = b;
+    cur_p0 = p0;
+    cur_end = p1;
+    cur_n = nb;
+  };
+
+  const uint32_t smem_base = lds_offset(smem);
+  // Page copies.  Latent instruction i of a batch that starts at the even row r0:
+  // rows r0 + 2i + h, LDS chunk n of the row takes global chunk n ^ swz(row) =
+  // (n ^ h) ^ cj with the wave-uniform cj below, so one per-lane register serves all.
+  // RoPE instruction i: rows r0 + 8i + lane/8, LDS chunk lane%8 takes global chunk
+  // (lane%8) ^ rswz(row) = (lane%8) ^ ((lane/16) & 3) ^ 4 (i & 1).
+  const uint32_t lat_v = (uint32_t)((((n ^ h) << 4)) | (h << 9));
+  const uint32_t rope_v = (uint32_t)((lane >> 3) * (kDr * 2) + (((lane & 7) ^ ((lane >> 4) & 3)) << 4));
+  auto page_ok = [&](int page) { return page >= 0 && page < a.num_pages; };
+  auto copy_latent = [&](int kb, int page, int r0, auto rows) {
+    if (!page_ok(page)) page = 0;
+    const uint8_t* src = a.kv_latent + (int64_t)page * kLatBytes + r0 * kDc;
+    const uint32_t dst = smem_base + (kb % kLatStages) * kLatBytes + r0 * kDc;
+#pragma unroll
+    for (int i = 0; i < decltype(rows)::value / 2; ++i) {
+      const uint32_t cj = (uint32_t)(swz(r0 + 2 * i) << 4);
+      g2lds16_so(src + 2 * i * kDc, lat_v ^ cj, dst + 1024 * i);
+    }
+  };
+  auto copy_rope_scale = [&](int kb, int page, int r0, auto rows) {
+    if (!page_ok(page)) page = 0;
+    const uint8_t* rp = reinterpret_cast<const uint8_t*>(a.k_rope) + (int64_t)page * kRopeBytes + r0 * (kDr * 2);
+    const uint8_t* sc = reinterpret_cast<const uint8_t*>(a.kv_scale) + (int64_t)page * kScBytes + r0 * 4;
+    const uint32_t dst = smem_base + kRsBase + (kb % kRsStages) * kRsBytes;
+#pragma unroll
+    for (int i = 0; i < decltype(rows)::value / 8; ++i)
+      g2lds16_so(rp + 8 * i * (kDr * 2), rope_v ^ (uint32_t)((i & 1) << 6), dst + r0 * (kDr * 2) + 1024 * i);
+    if (lane < decltype(rows)::value) g2lds4_so(sc, (uint32_t)(4 * lane), dst + kRopeBytes + 4 * r0);
+  };
+  // page-table cursor (scalar): blocks are asked for in nondecreasing order
+  int ib = cur_b, ib_lo = cur_p0, ib_hi = cur_end;
+  auto page_entry = [&](int kb) -> const int32_t* {
+    const int gb = gstart + kb;
+    while (unlikely(gb >= ib_hi)) {                          // skips sequences without blocks
+      ++ib;
+      ib_lo = ib_hi;
+      ib_hi = prefix[ib + 1];
+    }
+    return page_table + (int64_t)ib * a.max_pages + (gb - ib_lo);
+  };
+
+  if (w < 4) {
+    // ======================= QK / softmax waves ==============================
+    const int rq = w & 1, par = w >> 1;
+    const bool computes = RT == 2 || rq == 0;      // forms logits and codes
+    const bool copies = RT == 2 || rq == 1;        // copies pages
+    if (lane == 0) flag_store(xf + w, computes ? 0 : 0x7FFFFFFF);   // ordered before any wait by the first barrier
+    const int row = 64 * g + 32 * (RT == 2 ? rq : 0) + n;   // query row of this lane within the sequence
+    const int lrow = 32 * (RT == 2 ? rq : 0) + n;
+    const bool row_ok = row < a.R;
+    const float sl2 = a.sl2;
+    float cq = 0.f;                 // sigma_q
+    v8i qv[8];                      // q8 bytes 64s + 32h .. +31: the B operand of FP8 K-step s
+    v4i qr[4];                      // q_rope elements 16s + 8h .. +7
+    int vis = 0;
+    // per-lane LDS byte offsets inside a stage: latent chunk of K-step s, half c of token
+    // tile t: 16384 t + ((koff ^ 16 c) ^ 64 s); RoPE chunk of step s: 4096 t + roff[s]
+    const uint32_t koff = (uint32_t)(n * kDc + (((2 * h) ^ swz(n)) << 4));
+    uint32_t roff[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) roff[s] = (uint32_t)(n * (kDr * 2) + (((2 * s + h) ^ rswz(n)) << 4));
+    const uint32_t soff = (uint32_t)(kRopeBytes + 16 * h);
+
+    // queries and visible tokens of the piece cur_*
+    auto load_q = [&]() {
+      vis = a.causal ? cur_n - a.q_len + 1 + row / a.H : cur_n;
+      if (row_ok) {
+        const int64_t qrow = (int64_t)cur_b * a.R + row;
+        const v4i* src = reinterpret_cast<const v4i*>(a.q8 + qrow * kDc);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+          const v4i lo4 = src[4 * s + 2 * h], hi4 = src[4 * s + 2 * h + 1];
+          qv[s] = v8i{lo4[0], lo4[1], lo4[2], lo4[3], hi4[0], hi4[1], hi4[2], hi4[3]};
+        }
+        const v4i* rsrc = reinterpret_cast<const v4i*>(a.q_rope + qrow * kDr);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) qr[s] = rsrc[2 * s + h];
+        cq = a.sq[qrow];
+      } else {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) qv[s] = v8i{0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) qr[s] = v4i{0, 0, 0, 0};
+        cq = 0.f;
+      }
+    };
+
+    // Page ids come through the copy path rather than the scalar cache: a scalar load
+    // shares its wait counter with the LDS reads, so an LDS wait would also wait for a full
+    // memory round trip under the copy traffic.  A wave requests (one lane, one dword) the
+    // id of block j+4 with its copies of period j, into slot (j+4) % 4 of its ring, and reads
+    // it two periods later.
+    const uint32_t pg_ring = smem_base + kXpBase + 16 * w;
+    const int* pg_ring_p = reinterpret_cast<const int*>(smem + kXpBase + 16 * w);
+    auto request_page = [&](int kb) {
+      const int32_t* e = page_entry(min(kb, nblocks - 1));   // cursor update in uniform control flow
+      if (lane == 0) g2lds4_so(reinterpret_cast<const uint8_t*>(e), 0u, pg_ring + 4 * (kb & 3));
+    };
+    // Copies of period j, of block j+2 (the PV waves have copied block 2 and block 3's
+    // latent).  RT = 2: half the page, in the second period of the wave's block, behind its
+    // publication.  RT = 1: a copying wave takes half the page in either period.  The
+    // request for the id of block j+4 goes first: kOps requests in all, kOpsRs without the
+    // latent, 1 without a copy.
+    constexpr int kHalf = 32;                      // rows
+    constexpr int kOpsRs = 1 + kHalf / 8 + 1, kOps = kOpsRs + kHalf / 2;
+    auto copy_ahead = [&](int j, bool second) -> bool {   // returns whether the page is bad
+      const int pg = __builtin_amdgcn_readfirstlane(pg_ring_p[(j + 2) & 3]);
+      request_page(j + 4);
+      if (copies && j > 0 && (RT == 1 || second)) {
+        const int r0 = (RT == 2 ? rq : second) ? kHalf : 0;
+        copy_rope_scale(j + 2, pg, r0, std::integral_constant<int, kHalf>{});
+        if (j > 1) copy_latent(j + 2, pg, r0, std::integral_constant<int, kHalf>{});
+      }
+      return !page_ok(pg);
+    };
+    // Waits (loads complete in issue order): what this wave copied or asked for two periods
+    // ago is in, its requests of the last period may still be on their way.  block: the one
+    // that the last period's requests were for; second: they were those of a second period.
+    auto wait_older = [&](int block, bool second) {
+      if (unlikely(block >= nblocks)) wait_vmcnt<0>();
+      else if (!copies || (RT == 2 && !second)) wait_vmcnt<1>();
+      else if (unlikely(block == 3)) wait_vmcnt<kOpsRs>();
+      else wait_vmcnt<kOps>();
+    };
+    // Prologue: the ids that the wave needs first, its first block (half of it with RT = 2),
+    // its first queries.
+    bool bad = false;                              // the page of block k had an id out of range
+    if (par < nblocks) {
+      const int pg = *page_entry(par);
+      bad = !page_ok(pg);
+      request_page(par + 2);
+      request_page(par + 3);
+      if (copies) {
+        using First = std::integral_constant<int, RT == 2 ? 32 : 64>;
+        copy_rope_scale(par, pg, RT == 2 ? 32 * rq : 0, First{});
+        copy_latent(par, pg, RT == 2 ? 32 * rq : 0, First{});
+      }
+      if (gstart + par >= cur_end) seek(gstart + par);
+      if (computes) load_q();
+    }
+    wait_vmcnt<0>();
+    if (par == 1) barrier_vm_lgkm0<63>();          // period 0
+    int k = par;
+    for (; k < nblocks; k += 2) {
+      if (k >= 2) wait_older(k + 1, true);         // id of block k+2 (RT = 1: part of page k)
+      barrier_vm_lgkm0<63>();
+      const int gb = gstart + k;
+      const bool bad_next = k + 2 < nblocks ? copy_ahead(k, false) : false;
+      float pp[32], sk[32];
+      bool first = false;
+      if (computes) {
+        const uint32_t st = smem_base + (uint32_t)((k % kLatStages) * kLatBytes);      // latent of block k
+        const uint8_t* sr = smem + kRsBase + (k % kRsStages) * kRsBytes;               // its RoPE and scales
+        typedef __attribute__((address_space(3))) const v4i lds_cv4i;
+        auto ld = [&](uint32_t addr) -> v4i { return *(lds_cv4i*)(uintptr_t)addr; };
+        // ---- S^T tiles = K . Q^T: the RoPE products of both tiles, then the content
+        // products with six K-steps of operands in flight
+        v4i kr[2][4];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+#pragma unroll
+          for (int s = 0; s < 4; ++s) kr[t][s] = *reinterpret_cast<const v4i*>(sr + 4096 * t + roff[s]);
+        }
+        constexpr int kSlots = 6;
+        v4i kc[kSlots][2];
+        const uint32_t kb0 = st + koff, kb1 = kb0 ^ 16u;
+        auto load_k = [&](int i) {                   // step i = 8 t + s
+          const uint32_t x = (uint32_t)((i & 7) << 6), o = (uint32_t)((i >> 3) * 16384);
+          kc[i % kSlots][0] = ld((kb0 ^ x) + o);
+          kc[i % kSlots][1] = ld((kb1 ^ x) + o);
+        };
+#pragma unroll
+        for (int i = 0; i < kSlots; ++i) load_k(i);
+        __builtin_amdgcn_sched_barrier(0);
+        v16f accR[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          accR[t] = v16f{0};
+#pragma unroll
+          for (int s = 0; s < 4; ++s) accR[t] = mfma_bf16_32x32x16(kr[t][s], qr[s], accR[t]);
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          v16f c = v16f{0};
+#pragma unroll
+          for (int s = 0; s < 8; ++s) {
+            const int i = 8 * t + s;
+            const v4i lo = kc[i % kSlots][0], hi = kc[i % kSlots][1];
+            c = mfma_f8_32x32x64(v8i{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]}, qv[s], c);
+            if (i + kSlots < 16) load_k(i + kSlots);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          // raw logit u = sigma_q sigma_K acc_c + acc_r; s = tau log2(e) u enters the
+          // exponentials through one fma each.  Element 16t + 4q + v is token
+          // 32t + 8q + 4h + v.
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const v4f s4 = *reinterpret_cast<const v4f*>(sr + soff + 128 * t + 32 * q);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              sk[16 * t + 4 * q + v] = s4[v];
+              pp[16 * t + 4 * q + v] = fmaf(c[4 * q + v], cq * s4[v], accR[t][4 * q + v]);
+            }
+          }
+        }
+        const int blk = gb - cur_p0;
+        first = gb == (cur_p0 > gstart ? cur_p0 : gstart);   // the row state starts afresh
+        const bool tail = (blk + 1) * kPage > vis;   // some token of this block is hidden from this row
+        if (unlikely(tail)) {
+          // hidden tokens and stale slots past the sequence end: logit -inf, scale 0
+#pragma unroll
+          for (int i = 0; i < 32; ++i) {
+            const int j = blk * kPage + 32 * (i >> 4) + 8 * ((i >> 2) & 3) + 4 * h + (i & 3);
+            const bool vis_j = j < vis;
+            pp[i] = vis_j ? pp[i] : -INFINITY;
+            sk[i] = vis_j ? sk[i] : 0.0f;
+          }
+        }
+        // a later piece's queries, once this block's products are done with the present ones
+        // (waited for here: a wait on the straight path would drain the page copies too)
+        if (k + 2 < nblocks && unlikely(gb + 2 >= cur_end)) {
+          seek(gb + 2);
+          load_q();
+          wait_vmcnt<0>();
+        }
+      }
+      if (k >= 2) wait_older(k + 2, false);        // this wave's part of page k+1, id of block k+3
+      barrier_vm_lgkm0<63>();                      // period k+1
+      if (computes) {
+        float m = -INFINITY, sp = 1.0f, l = 0.0f;
+        if (!first) {                              // the state after block k-1, published in period k
+          const v4f prev = *reinterpret_cast<const v4f*>(xg + lrow * 4);
+          l = prev[1];
+          m = prev[2];
+          sp = prev[3];
+        }
+        // ---- block statistics of this row (32 logits here, 32 in lane ^ 32)
+        // (maxima that propagate NaN: no logit is NaN here -- hidden and stale slots are -inf,
+        // and a bad page marks the piece NaN whatever its logits)
+        float mx = vmax(vmax16(*reinterpret_cast<const float(*)[16]>(pp)), vmax16(*reinterpret_cast<const float(*)[16]>(pp + 16)));
+        const float mb = xhalf_vmax(mx) * sl2;       // block max of this row (log2 units)
+        v4i mine[2] = {v4i{0, 0, 0, 0}, v4i{0, 0, 0, 0}};
+        float gam = 1.0f;
+        if (likely(mb > -INFINITY)) {                // the row sees a token of this block
+          const float m_new = vmax(m, mb);
+          float e[32];
+#pragma unroll
+          for (int i = 0; i < 32; ++i) e[i] = __builtin_amdgcn_exp2f(fmaf(pp[i], sl2, -m_new));
+#pragma unroll
+          for (int i = 0; i < 32; ++i) pp[i] = e[i] * sk[i];
+          float es[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) es[i] = (e[4 * i] + e[4 * i + 1]) + (e[4 * i + 2] + e[4 * i + 3]);
+          float esum = ((es[0] + es[1]) + (es[2] + es[3])) + ((es[4] + es[5]) + (es[6] + es[7]));
+          float pmax = vmax(vmax16(*reinterpret_cast<const float(*)[16]>(pp)), vmax16(*reinterpret_cast<const float(*)[16]>(pp + 16)));
+          esum = xhalf_sum(esum);
+          pmax = xhalf_vmax(pmax);
+          // (reciprocals instead of divisions: off by at most an ulp, far inside the
+          // rounding slack of the probability codes)
+          const float sP = fmaxf(pmax * (1.0f / kFp8Max), kEps);
+          const float inv = __builtin_amdgcn_rcpf(sP);
+          gam = __builtin_amdgcn_exp2f(m - m_new) * (sp * inv);
+          l = gam * l + esum * inv;
+          m = m_new;
+          sp = sP;
+#pragma unroll
+          for (int d = 0; d < 8; ++d) {
+            int wd = cvt_pk_e4m3(pp[4 * d + 0] * inv, pp[4 * d + 1] * inv, 0, false);
+            wd = cvt_pk_e4m3(pp[4 * d + 2] * inv, pp[4 * d + 3] * inv, wd, true);
+            mine[d >> 2][d & 3] = wd;
+          }
+        }
+        if (unlikely(bad)) l = __builtin_nanf("");   // stays NaN to the end of the piece
+        // the lane's 32 codes at bytes 32h .. +31 of the row (logical; 16-byte chunk c sits at
+        // chunk c ^ ((row >> 2) & 3)); the PV waves have read the previous block's before
+        // this period's barrier
+        const int cs = (n >> 2) & 3;
+        *reinterpret_cast<v4i*>(xc + lrow * 64 + 16 * ((2 * h) ^ cs)) = mine[0];
+        *reinterpret_cast<v4i*>(xc + lrow * 64 + 16 * ((2 * h + 1) ^ cs)) = mine[1];
+        if (h == 0) *reinterpret_cast<v4f*>(xg + lrow * 4) = v4f{gam, l, m, sp};
+        lds_wait_all();
+        if (lane == 0) flag_store(xf + rq, k + 1);   // block k published
+      }
+      if (k + 3 < nblocks) copy_ahead(k + 1, true);
+      bad = bad_next;
+    }
+    for (; k < nblocks + 2; ++k) barrier_vm_lgkm0<63>();   // the periods in which only others work
+  } else {
+    // =========================== PV waves ====================================
+    const int dq = w - 4;                          // dims 128dq..128dq+127
+    // prologue copies: 16 rows per wave of block 2, and of block 3's latent (its RoPE
+    // stage is block 0's until period 1, when the QK waves copy it)
+    if (nblocks > 2) {
+      const int pg2 = *page_entry(2);
+      copy_latent(2, pg2, 16 * dq, std::integral_constant<int, 16>{});
+      copy_rope_scale(2, pg2, 16 * dq, std::integral_constant<int, 16>{});
+      if (nblocks > 3) copy_latent(3, *page_entry(3), 16 * dq, std::integral_constant<int, 16>{});
+    }
+    // O[RT T + r]: O^T tile of dims 128dq + 32T.. and row tile r
+    v16f O[4 * RT];
+#pragma unroll
+    for (int T = 0; T < 4 * RT; ++T) O[T] = v16f{0};
+    // transposed V reads: 16-lane group g16 of half h reads 8 token rows x 16 bytes;
+    // lane pair (2i, 2i+1) supplies row i.  K index 32h + 8c + i of the PV product
+    // is token 32(c>>1) + 16(c&1) + 8(i>>2) + 4h + (i&3): the token whose code the
+    // QK waves store at byte 32h + 8c + i of the row.  The byte offset of tile T,
+    // read c inside a stage is tr_off[c] ^ (T << 5): the row offset, byte half and
+    // swizzled chunk ((8dq + g16) ^ swz(tok)) ^ 2T occupy disjoint bits, and so
+    // does the stage base.
+    const int q16 = lane & 15, tri = q16 >> 1, trb = q16 & 1, g16 = (lane >> 4) & 1;
+    uint32_t tr_off[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int tok = 32 * (c >> 1) + 16 * (c & 1) + 8 * (tri >> 2) + 4 * h + (tri & 3);
+      tr_off[c] = (uint32_t)(tok * kDc + 8 * trb) | (uint32_t)(((8 * dq + g16) ^ swz(tok)) << 4);
+    }
+    v2i rv[4][4];                 // V^T tiles of the pending block
+    v8i P[RT];                    // its codes, per row tile
+    v4f gl[RT];                   // its per-row state {gamma, l, m, sigma_P}
+    bool cur_bad = false;
+    int cur_blk0 = gstart - cur_p0;
+    barrier_vm_lgkm0<63>();                        // period 0
+    for (int k = 0;; ++k) {                        // period k+1: products of block k-1, operands of block k
+      // (the prologue copies of blocks 2 and 3 land before periods 2 and 3)
+      if (unlikely(k == 1 || k == 2)) {
+        if (k == 1 && nblocks > 3) wait_vmcnt<8>();
+        else wait_vmcnt<0>();
+      }
+      barrier_vm_lgkm0<63>();
+      if (likely(k > 0)) {
+        // ---- PV of block k-1 --------------------------------------------------
+        // each accumulator is rescaled right before its product, so that the
+        // multiplies of the next one run while the matrix core works
+#pragma unroll
+        for (int T = 0; T < 4; ++T) {
+          const v8i A = v8i{rv[T][0][0], rv[T][0][1], rv[T][1][0], rv[T][1][1],
+                            rv[T][2][0], rv[T][2][1], rv[T][3][0], rv[T][3][1]};
+#pragma unroll
+          for (int r = 0; r < RT; ++r) {
+            O[RT * T + r] *= gl[r][0];
+            O[RT * T + r] = mfma_f8_32x32x64(A, P[r], O[RT * T + r]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        // ---- end of a piece: write the normalized partial output and LSE ----
+        // (one 16-byte store at a time; a bad piece makes the multiplier NaN)
+        if (unlikely(k == nblocks || gstart + k >= cur_end)) {
+          const int64_t pid = a.chunk_blocks == 0 ? (int64_t)unit + cur_b
+                                                  : (int64_t)cur_b * a.num_splits + cur_blk0 / a.chunk_blocks;
+          const bool whole = cur_blk0 == 0 && gstart + k >= cur_end;   // the piece is its whole sequence
+#pragma unroll
+          for (int r = 0; r < RT; ++r) {
+            float inv, lse;
+            piece_row_result(gl[r], cur_bad, inv, lse);
+            store_piece_tile<RT, false>(a, O, r, inv, lse, 64 * g + 32 * r + n, dq, h, pid, cur_b, whole);
+          }
+#pragma unroll
+          for (int T = 0; T < 4 * RT; ++T) O[T] = v16f{0};
+        }
+      }
+      if (unlikely(k == nblocks)) break;
+
+      // ---- block k: piece bookkeeping ----------------------------------------
+      const int gb = gstart + k;
+      if (unlikely(gb >= cur_end)) {
+        seek(gb);
+        cur_blk0 = gb - cur_p0;
+        cur_bad = false;
+      }
+      const int valid = min(kPage, cur_n - (gb - cur_p0) * kPage);
+      uint8_t* stp = smem + (k % kLatStages) * kLatBytes;
+      if (unlikely(valid < kPage)) {
+        // last page of a sequence: clear the bytes of the slots past its end that
+        // this wave reads (stale data could hold NaN codes; their probability
+        // codes are 0).  The QK waves mask these slots whatever they hold.
+        const int nz = (kPage - valid) * 8;
+        for (int i = lane; i < nz; i += 64) {
+          const int t = valid + (i >> 3);
+          const int c = 8 * dq + (i & 7);
+          *reinterpret_cast<v4i*>(stp + t * kDc + ((c ^ swz(t)) << 4)) = v4i{0, 0, 0, 0};
+        }
+      }
+      // V^T tiles of block k
+      const uint32_t st_lds = smem_base + (k % kLatStages) * kLatBytes;
+#pragma unroll
+      for (int T = 0; T < 4; ++T) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) rv[T][c] = lds_read_tr8_at((st_lds | tr_off[c]) ^ (uint32_t)(T << 5));
+      }
+      // codes and state of block k, once the QK waves have published them
+      {
+        // one exit for both ends of the wait (the flags seen, or the bound reached),
+        // decided again from the last poll: codes never published, or a zero
+        // bound, mark the piece, which then comes out NaN
+        v4i f4;
+        int spin = 0;
+        auto past = [&]() { return f4[0] > k && f4[1] > k; };
+        do {
+          f4 = flag_load4(xf);
+        } while (!past() && ++spin < a.spin_limit);
+        if (!past() || a.spin_limit <= 0) cur_bad = true;
+      }
+      asm volatile("" ::: "memory");
+      // B operand of row tile r: bytes 32h .. 32h+31 of row 32r + n (the K order
+      // of the PV product, see the transposed reads)
+      const int cs = (n >> 2) & 3;                  // chunk swizzle of rows n and 32 + n
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        gl[r] = *reinterpret_cast<const v4f*>(xg + (n + 32 * r) * 4);
+        const v4i c0 = *reinterpret_cast<const v4i*>(xc + (32 * r + n) * 64 + 16 * ((2 * h) ^ cs));
+        const v4i c1 = *reinterpret_cast<const v4i*>(xc + (32 * r + n) * 64 + 16 * ((2 * h + 1) ^ cs));
+        P[r] = v8i{c0[0], c0[1], c0[2], c0[3], c1[0], c1[1], c1[2], c1[3]};
+      }
+      lds_wait_all();
+    }
+  }
+}
+
+}  // namespace
+
+hipError_t launch_decode_stagger(const DecodeArgs& a, hipStream_t stream) {
+  const int units = a.chunk_blocks == 0 ? a.num_splits : a.B * a.num_splits;
+  if (units <= 0) return hipSuccess;
+  const int64_t grid = (int64_t)((units + 7) / 8) * 8 * a.G;
+  if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
+  auto k = a.R <= 32 ? decode_stagger_kernel<1> : decode_stagger_kernel<2>;
+  hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(64 * kWaves), 0, stream, a, a.prefix, a.page_table, a.seq_lens);
+  return hipGetLastError();
+}
+
+}  // namespace snapmla

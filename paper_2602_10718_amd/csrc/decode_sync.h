@@ -1,0 +1,50 @@
+// Small pieces shared by the FP8 decode kernels: branch weights, the LDS handshake flags
+// and the per-row results at a piece end.
+#pragma once
+
+#include "snapmla_device.h"
+
+namespace snapmla {
+
+// Branch weights for the block layout: the rare cases of a period (a piece start
+// or end, a sequence's last page, the first and last periods) are laid out off the
+// straight path, which then runs with fewer taken branches.
+// (macros: the hint must sit in the branch condition itself to reach the layout)
+#define likely(c) __builtin_expect(!!(c), 1)
+#define unlikely(c) __builtin_expect(!!(c), 0)
+
+constexpr float kLn2 = 0.69314718055994531f;
+
+// Per-row results at a piece end from the published state {gamma, l, m, sigma_P} of
+// the row's last block: 1/l and LSE = ln 2 (m + log2(sigma_P l)) (m in log2 units;
+// Algorithm 1 finalisation); 0 and -inf for a row without tokens, NaN for a bad piece
+// (bad here, or a NaN l).
+__device__ __forceinline__ void piece_row_result(v4f gl, bool bad, float& inv, float& lse) {
+  const float lfin = gl[1];
+  const bool empty = lfin == 0.0f;
+  inv = empty ? 0.0f : 1.0f / lfin;
+  lse = empty ? -INFINITY : (gl[2] + log2f(gl[3] * lfin)) * kLn2;
+  if (bad) {
+    inv = __builtin_nanf("");
+    lse = __builtin_nanf("");
+  }
+}
+
+// Handshake flags in LDS.  A wave's LDS operations complete in issue order, so
+// a flag stored after lds_wait_all() is seen only after the data stored before it.
+// (the builtin rather than inline asm: the compiler's own wait-count pass then
+// knows that every LDS result is in, and inserts no later waits for them)
+__device__ __forceinline__ void lds_wait_all() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0); vmcnt and expcnt left alone
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void flag_store(int* f, int v) {
+  __hip_atomic_store(f, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// Four consecutive flags with one LDS read (an explicit LDS pointer: a generic one
+// would become a flat load, which queues behind the page copies).
+typedef __attribute__((address_space(3))) volatile v4i lds_flags4;
+__device__ __forceinline__ v4i flag_load4(const int* f) { return *(const lds_flags4*)(f); }
+
+}  // namespace snapmla

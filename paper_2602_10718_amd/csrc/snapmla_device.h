@@ -118,6 +118,11 @@ __device__ __forceinline__ float quad_vmax(float x) {
   r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return vmax(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
+// maximum over lanes i and i^32 (NaN-propagating)
+__device__ __forceinline__ float xhalf_vmax(float x) {
+  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return vmax(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
 // max over 16 values as five three-input maxima
 __device__ __forceinline__ float vmax16(const float (&v)[16]) {
   const float a = vmax3(v[0], v[1], v[2]), b = vmax3(v[3], v[4], v[5]), c = vmax3(v[6], v[7], v[8]);

@@ -87,7 +87,7 @@ struct DecodeArgs {
   const int32_t* prefix;
   const int32_t* desc;      // [units][kDescInts]
   const uint8_t* zero;
-  float* part_o;            // [pieces][rows_pad * 512]: rows, or part_tile_offset order (rows_pad > 64)
+  float* part_o;            // [pieces][rows_pad * 512] in part_tile_offset order
   float* part_lse;          // [pieces][rows_pad]
   int B, q_len, H, R, G, rows_pad, max_pages, num_pages, causal;
   int num_splits, chunk_blocks;  // chunk_blocks == 0: balanced plan over num_splits parts
@@ -116,15 +116,12 @@ __host__ __device__ inline bool seq_len_ok(int n, int q_len, int max_pages, int 
   return ok;
 }
 
-// Float32 offset of a partial-output element inside its piece's slot when the rows
-// form several 64-row groups (rows_pad > 64).  The order follows the PV waves'
-// accumulator tiles, so that each 16-byte store instruction of a wave writes 1 KiB of
-// consecutive memory: row group g (rows 64g..64g+63), dimension quarter dq (128
-// dimensions), row tile rt (32 rows), dimension tile T (32 dimensions), chunk pair q
-// (8 dimensions), then lane n + 32h, which holds row 64g + 32rt + n, dimensions
-// 128dq + 32T + 8q + 4h .. +3.  With one row group the slot keeps plain rows
-// ([64][512]): there the merge skips, row by row, the pieces whose weight underflows
-// to zero, which needs each row's partial in its own cache lines.
+// Float32 offset of a partial-output element inside its piece's slot.  The order follows
+// the PV waves' accumulator tiles, so that each 16-byte store instruction of a wave writes
+// 1 KiB of consecutive memory (plain rows cost 32 segments of 32 bytes): row group g (rows
+// 64g..64g+63), dimension quarter dq (128 dimensions), row tile rt (32 rows), dimension
+// tile T (32 dimensions), chunk pair q (8 dimensions), then lane n + 32h, which holds row
+// 64g + 32rt + n, dimensions 128dq + 32T + 8q + 4h .. +3.
 __host__ __device__ constexpr int64_t part_tile_offset(int g, int dq, int rt, int T, int q, int lane) {
   return (int64_t)g * 32768 + dq * 8192 + rt * 4096 + T * 1024 + q * 256 + lane * 4;
 }
@@ -160,6 +157,7 @@ hipError_t launch_append(const uint16_t* c_kv_new, const uint16_t* k_rope_new, c
 hipError_t launch_encode(const float* x, int64_t n, uint8_t* codes, hipStream_t stream);
 hipError_t launch_prep(const PrepArgs& a, hipStream_t stream);
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream);
+hipError_t launch_decode_stagger(const DecodeArgs& a, hipStream_t stream);
 hipError_t launch_combine(const CombineArgs& a, hipStream_t stream);
 hipError_t launch_fetch_dequant(const FetchArgs& a, hipStream_t stream);
 hipError_t launch_decode_bf16(const DecodeArgs& a, const uint16_t* kv_latent_bf16, hipStream_t stream);

@@ -1,0 +1,54 @@
+"""GPU: the staggered decode schedule at its edges.
+
+Ranges of one to a few blocks (prologue copies, the last two periods), ranges whose pieces are
+one block each (a wave of one parity skips pieces and reloads its queries every block, the row
+state starts afresh in every period), row counts at the edges of the 32-row tiles and both
+parities of every start.  Every row against the oracle (derived bounds and the tolerance of
+check_sequence).  A bad page id at any place of a sequence gives NaN rows for that sequence and
+leaves the others alone.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_10718_amd import workloads as wl
+from gpu_common import runner, reference, check_sequence
+
+pytestmark = pytest.mark.gpu
+
+LENS = [1, 64, 65, 130, 63, 0, 200, 3, 64, 321]
+
+
+@pytest.mark.parametrize("rows", [(1, 1), (16, 2), (17, 1), (32, 1), (33, 1), (64, 1), (40, 2)])
+@pytest.mark.parametrize("parts", [1, 2, 3, 5, 19])
+def test_short_ranges_and_one_block_pieces(rows, parts):
+    H, q_len = rows
+    lens = [n if n == 0 or n >= q_len else q_len for n in LENS]
+    w = wl.custom(B=len(lens), H=H, q_len=q_len, seq_lens=lens, causal=q_len == 2, seed=91, n_new=1)
+    run = runner(w, num_splits=parts)
+    run.out.fill_(12345.0)
+    run.step()
+    torch.cuda.synchronize()
+    assert not (run.out == 12345.0).any()
+    qn, qr = w.queries()
+    for b in range(len(lens)):
+        if lens[b]:
+            check_sequence(run, b, reference(w, b, qn, qr), label=f"stagger H{H} q{q_len} parts{parts}")
+        else:
+            assert (run.out[b] == 0).all() and torch.isneginf(run.lse[b]).all()
+
+
+@pytest.mark.parametrize("H", [16, 64])
+@pytest.mark.parametrize("place", [0, 1, 2, 3, 4, 7])
+def test_bad_page_marks_its_sequence_only(H, place):
+    w = wl.custom(B=3, H=H, q_len=1, seq_lens=[129, 64 * 7 + 5, 300], seed=92, n_new=0)
+    run = runner(w, num_splits=1)
+    run.step()
+    good = (run.out.clone(), run.lse.clone())
+    run.page_table[1, place] = w.num_pages
+    run.step()
+    torch.cuda.synchronize()
+    assert torch.isnan(run.out[1]).all() and torch.isnan(run.lse[1]).all()
+    for b in (0, 2):
+        assert torch.equal(run.out[b], good[0][b]) and torch.equal(run.lse[b], good[1][b])
