@@ -135,7 +135,9 @@ int snapmla_quantize_rows(const void* x, int64_t rows, uint8_t* codes, float* sc
  *                         may span several parts and a part several sequences;
  *                         with R <= 64 each sequence start counts as 4 extra
  *                         blocks, so parts that hold a sequence boundary get
- *                         up to 4 fewer blocks)
+ *                         up to 4 fewer blocks; batches with few blocks use
+ *                         fewer parts: the merge of a part costs as much as
+ *                         several blocks)
  *   kv_chunk_tokens  > 0: every sequence is cut into chunks of kv_chunk_tokens
  *                         (a multiple of 64); num_splits bounds the chunks per
  *                         sequence (sequences needing more are flagged NaN).

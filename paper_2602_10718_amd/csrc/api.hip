@@ -155,6 +155,7 @@ int decode_common(const void* q_nope, const void* q_rope, const void* kv_latent,
   p.desc = reinterpret_cast<int32_t*>(ws + L.desc);
   p.units = L.units;
   p.pad = L.pad;
+  p.plan_cost = snapmla::kPlanCost * (bf16_cache ? 2.0f : 1.0f) * 64.0f / (float)L.R;
   p.B = B;
   p.q_len = q_len;
   p.max_pages = max_pages;

@@ -38,8 +38,8 @@ struct Pieces {
 __device__ Pieces pieces_of(const CombineArgs& a, int b) {
   Pieces P;
   P.b = b;
-  P.W = a.num_splits;
   P.balanced = a.chunk_blocks == 0;
+  P.W = P.balanced ? a.ctrl[1] : a.num_splits;
   P.TV = a.prefix[a.B] + (int64_t)a.pad * a.B;
   const int p0 = a.prefix[b], p1 = a.prefix[b + 1];
   const int nb = p1 - p0;

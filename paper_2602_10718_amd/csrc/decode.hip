@@ -1,4 +1,6 @@
-// FP8 MLA decode kernel (Algorithm 1; Appendix D recurrences; Section 3.2).
+// FP8 MLA decode kernel (Algorithm 1; Appendix D recurrences; Section 3.2), every block's
+// codes within its own period: for the exact QK mode, and for several row groups over short
+// sequences (launch_decode; the other calls run decode_stagger.hip).
 //
 // One workgroup = 8 waves (two per SIMD) = 64 query rows of one row group x a
 // contiguous range of 64-token KV blocks (one page each).  The waves specialise:
@@ -75,6 +77,7 @@ constexpr int kLatBytes = kPage * kDc;          // 32768
 constexpr int kRopeBytes = kPage * kDr * 2;     // 8192
 constexpr int kScBytes = kPage * 4;             // 256
 constexpr int kRsBytes = kRopeBytes + kScBytes;  // RoPE + scale part of a page
+constexpr int kShortPages = 48;                 // see launch_decode
 constexpr int kLatStages = 4;
 constexpr int kRsStages = 3;
 constexpr int kRsBase = kLatStages * kLatBytes;   // LDS offset of the RoPE/scale ring
@@ -777,17 +780,22 @@ __global__ __launch_bounds__(512, 1) void decode_kernel(DecodeArgs a, const int3
 }
 
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream) {
-  if (!a.qk_exact) return launch_decode_stagger(a, stream);
   const int units = a.chunk_blocks == 0 ? a.num_splits : a.B * a.num_splits;
   if (units <= 0) return hipSuccess;
   const int64_t grid = (int64_t)((units + 7) / 8) * 8 * a.G;
   if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
+  // The staggered schedule (decode_stagger.hip) takes the FP8 products, but for several row
+  // groups over short sequences: a range that crosses into another sequence costs it ~4.5 us
+  // against 2.3 us here, which 16-block sequences do not earn back (116 x 128 heads, 125-2094
+  // tokens: decode 53.2 against 44.2 us; from ~50 blocks a sequence on the two are even, and
+  // B128 H128 q2, 1K-16K, takes 410 against 437 us).  The page table bounds the lengths.
+  const bool short_groups = a.G > 1 && a.max_pages <= kShortPages;
+  if (!a.qk_exact && !short_groups) return launch_decode_stagger(a, stream);
   // With several row groups the workgroups of a unit share its pages through L2 and
   // the period is bound by the waves' own work: there the copies go first and the
   // products of block k-1 precede the transposed reads of block k (kRotate).  With
   // one row group the pages come from HBM and the products go first.
-  auto k = a.G > 1 ? (a.qk_exact ? decode_kernel<true, true> : decode_kernel<true, false>)
-                   : (a.qk_exact ? decode_kernel<false, true> : decode_kernel<false, false>);
+  auto k = !a.qk_exact ? decode_kernel<true, false> : a.G > 1 ? decode_kernel<true, true> : decode_kernel<false, true>;
   hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(64 * kWaves), 0, stream, a, a.prefix, a.page_table, a.seq_lens);
   return hipGetLastError();
 }

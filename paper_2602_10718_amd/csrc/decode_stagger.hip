@@ -119,12 +119,14 @@ __global__ __launch_bounds__(512, 1) void decode_stagger_kernel(DecodeArgs a, co
   const int gstart = dsc[kDescStart], gend = dsc[kDescEnd];
   if (gstart >= gend) return;
   const int nblocks = gend - gstart;
-  // piece of the wave's current block (scalar)
-  int cur_b = dsc[kDescSeq], cur_p0 = dsc[kDescP0], cur_end = dsc[kDescP1], cur_n = dsc[kDescLen];
-  // moves on to the piece that holds global block gb >= cur_end (the three loads of the
+  struct Piece {                                  // a sequence that the range meets (scalar)
+    int b, p0, end, n;                            // its number, first and end block, length in tokens
+  };
+  Piece cur = {dsc[kDescSeq], dsc[kDescP0], dsc[kDescP1], dsc[kDescLen]};   // of the wave's current block
+  // moves p on to the piece that holds global block gb >= p.end (the three loads of the
   // usual case, the next sequence, are issued together: one memory round trip)
-  auto seek = [&](int gb) {
-    int b = cur_b + 1;
+  auto seek = [&](Piece& p, int gb) {
+    int b = p.b + 1;
     int p0 = prefix[b], p1 = prefix[b + 1], nb = seq_lens[b];
     asm volatile("" ::"s"(nb));                   // keeps the length load beside the prefix loads
     while (p1 <= gb) {
@@ -133,10 +135,7 @@ __global__ __launch_bounds__(512, 1) void decode_stagger_kernel(DecodeArgs a, co
       p1 = prefix[b + 1];
       nb = seq_lens[b];
     }
-    cur_b = b;
-    cur_p0 = p0;
-    cur_end = p1;
-    cur_n = nb;
+    p = Piece{b, p0, p1, nb};
   };
 
   const uint32_t smem_base = lds_offset(smem);
@@ -169,7 +168,7 @@ __global__ __launch_bounds__(512, 1) void decode_stagger_kernel(DecodeArgs a, co
     if (lane < decltype(rows)::value) g2lds4_so(sc, (uint32_t)(4 * lane), dst + kRopeBytes + 4 * r0);
   };
   // page-table cursor (scalar): blocks are asked for in nondecreasing order
-  int ib = cur_b, ib_lo = cur_p0, ib_hi = cur_end;
+  int ib = cur.b, ib_lo = cur.p0, ib_hi = cur.end;
   auto page_entry = [&](int kb) -> const int32_t* {
     const int gb = gstart + kb;
     while (unlikely(gb >= ib_hi)) {                          // skips sequences without blocks
@@ -202,11 +201,11 @@ __global__ __launch_bounds__(512, 1) void decode_stagger_kernel(DecodeArgs a, co
     for (int s = 0; s < 4; ++s) roff[s] = (uint32_t)(n * (kDr * 2) + (((2 * s + h) ^ rswz(n)) << 4));
     const uint32_t soff = (uint32_t)(kRopeBytes + 16 * h);
 
-    // queries and visible tokens of the piece cur_*
-    auto load_q = [&]() {
-      vis = a.causal ? cur_n - a.q_len + 1 + row / a.H : cur_n;
+    // queries and visible tokens of a piece
+    auto load_q = [&](const Piece& p) {
+      vis = a.causal ? p.n - a.q_len + 1 + row / a.H : p.n;
       if (row_ok) {
-        const int64_t qrow = (int64_t)cur_b * a.R + row;
+        const int64_t qrow = (int64_t)p.b * a.R + row;
         const v4i* src = reinterpret_cast<const v4i*>(a.q8 + qrow * kDc);
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
@@ -276,9 +275,14 @@ __global__ __launch_bounds__(512, 1) void decode_stagger_kernel(DecodeArgs a, co
         copy_rope_scale(par, pg, RT == 2 ? 32 * rq : 0, First{});
         copy_latent(par, pg, RT == 2 ? 32 * rq : 0, First{});
       }
-      if (gstart + par >= cur_end) seek(gstart + par);
-      if (computes) load_q();
+      if (gstart + par >= cur.end) seek(cur, gstart + par);
+      if (computes) load_q(cur);
     }
+    Piece next = cur;                              // the piece of the wave's next block, k+2
+    auto look_ahead = [&](int kb) {
+      if (kb < nblocks && unlikely(gstart + kb >= next.end)) seek(next, gstart + kb);
+    };
+    look_ahead(par + 2);
     wait_vmcnt<0>();
     if (par == 1) barrier_vm_lgkm0<63>();          // period 0
     int k = par;
@@ -344,8 +348,8 @@ __global__ __launch_bounds__(512, 1) void decode_stagger_kernel(DecodeArgs a, co
             }
           }
         }
-        const int blk = gb - cur_p0;
-        first = gb == (cur_p0 > gstart ? cur_p0 : gstart);   // the row state starts afresh
+        const int blk = gb - cur.p0;
+        first = gb == (cur.p0 > gstart ? cur.p0 : gstart);   // the row state starts afresh
         const bool tail = (blk + 1) * kPage > vis;   // some token of this block is hidden from this row
         if (unlikely(tail)) {
           // hidden tokens and stale slots past the sequence end: logit -inf, scale 0
@@ -357,17 +361,13 @@ __global__ __launch_bounds__(512, 1) void decode_stagger_kernel(DecodeArgs a, co
             sk[i] = vis_j ? sk[i] : 0.0f;
           }
         }
-        // a later piece's queries, once this block's products are done with the present ones
-        // (waited for here: a wait on the straight path would drain the page copies too)
-        if (k + 2 < nblocks && unlikely(gb + 2 >= cur_end)) {
-          seek(gb + 2);
-          load_q();
-          wait_vmcnt<0>();
-        }
       }
       if (k >= 2) wait_older(k + 2, false);        // this wave's part of page k+1, id of block k+3
       barrier_vm_lgkm0<63>();                      // period k+1
       if (computes) {
+        // a later piece's queries for the wave's next block: this block's products are done with
+        // the present ones, and the softmax covers the loads
+        if (unlikely(next.b != cur.b)) load_q(next);
         float m = -INFINITY, sp = 1.0f, l = 0.0f;
         if (!first) {                              // the state after block k-1, published in period k
           const v4f prev = *reinterpret_cast<const v4f*>(xg + lrow * 4);
@@ -421,9 +421,14 @@ __global__ __launch_bounds__(512, 1) void decode_stagger_kernel(DecodeArgs a, co
         if (h == 0) *reinterpret_cast<v4f*>(xg + lrow * 4) = v4f{gam, l, m, sp};
         lds_wait_all();
         if (lane == 0) flag_store(xf + rq, k + 1);   // block k published
+        // new queries are in before the copies go out (a wait at their first use would drain
+        // those); otherwise only the id request of the last period can be outstanding
+        wait_vmcnt<0>();
       }
       if (k + 3 < nblocks) copy_ahead(k + 1, true);
       bad = bad_next;
+      cur = next;
+      look_ahead(k + 4);                           // (its scalar loads wait here, off the products' path)
     }
     for (; k < nblocks + 2; ++k) barrier_vm_lgkm0<63>();   // the periods in which only others work
   } else {
@@ -459,7 +464,8 @@ __global__ __launch_bounds__(512, 1) void decode_stagger_kernel(DecodeArgs a, co
     v8i P[RT];                    // its codes, per row tile
     v4f gl[RT];                   // its per-row state {gamma, l, m, sigma_P}
     bool cur_bad = false;
-    int cur_blk0 = gstart - cur_p0;
+    int cur_blk0 = gstart - cur.p0;
+    Piece next = cur;                              // the piece of block k+1
     barrier_vm_lgkm0<63>();                        // period 0
     for (int k = 0;; ++k) {                        // period k+1: products of block k-1, operands of block k
       // (the prologue copies of blocks 2 and 3 land before periods 2 and 3)
@@ -483,32 +489,23 @@ __global__ __launch_bounds__(512, 1) void decode_stagger_kernel(DecodeArgs a, co
             __builtin_amdgcn_sched_barrier(0);
           }
         }
-        // ---- end of a piece: write the normalized partial output and LSE ----
-        // (one 16-byte store at a time; a bad piece makes the multiplier NaN)
-        if (unlikely(k == nblocks || gstart + k >= cur_end)) {
-          const int64_t pid = a.chunk_blocks == 0 ? (int64_t)unit + cur_b
-                                                  : (int64_t)cur_b * a.num_splits + cur_blk0 / a.chunk_blocks;
-          const bool whole = cur_blk0 == 0 && gstart + k >= cur_end;   // the piece is its whole sequence
-#pragma unroll
-          for (int r = 0; r < RT; ++r) {
-            float inv, lse;
-            piece_row_result(gl[r], cur_bad, inv, lse);
-            store_piece_tile<RT, false>(a, O, r, inv, lse, 64 * g + 32 * r + n, dq, h, pid, cur_b, whole);
-          }
-#pragma unroll
-          for (int T = 0; T < 4 * RT; ++T) O[T] = v16f{0};
-        }
       }
-      if (unlikely(k == nblocks)) break;
-
-      // ---- block k: piece bookkeeping ----------------------------------------
+      // ---- end of a piece, whose last block was k-1: the normalized output and LSE (one
+      // 16-byte store at a time; a bad piece makes the multiplier NaN).  Written once the QK
+      // waves have published block k, so behind their page copies in the memory pipe
+      // (128 KiB a workgroup ahead of them delayed those and so a later period).
+      const bool ended = k > 0 && (k == nblocks || gstart + k >= cur.end);
+      const int end_b = cur.b, end_end = cur.end, end_blk0 = cur_blk0;
+      const bool end_bad = cur_bad;
       const int gb = gstart + k;
-      if (unlikely(gb >= cur_end)) {
-        seek(gb);
-        cur_blk0 = gb - cur_p0;
+      if (likely(k < nblocks)) {
+      // ---- block k: piece bookkeeping ----------------------------------------
+      if (unlikely(gb >= cur.end)) {
+        cur = next;
+        cur_blk0 = gb - cur.p0;
         cur_bad = false;
       }
-      const int valid = min(kPage, cur_n - (gb - cur_p0) * kPage);
+      const int valid = min(kPage, cur.n - (gb - cur.p0) * kPage);
       uint8_t* stp = smem + (k % kLatStages) * kLatBytes;
       if (unlikely(valid < kPage)) {
         // last page of a sequence: clear the bytes of the slots past its end that
@@ -541,7 +538,22 @@ __global__ __launch_bounds__(512, 1) void decode_stagger_kernel(DecodeArgs a, co
         } while (!past() && ++spin < a.spin_limit);
         if (!past() || a.spin_limit <= 0) cur_bad = true;
       }
+      }
       asm volatile("" ::: "memory");
+      if (unlikely(ended)) {
+        const int64_t pid = a.chunk_blocks == 0 ? (int64_t)unit + end_b
+                                                : (int64_t)end_b * a.num_splits + end_blk0 / a.chunk_blocks;
+        const bool whole = end_blk0 == 0 && gstart + k >= end_end;   // the piece is its whole sequence
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+          float inv, lse;
+          piece_row_result(gl[r], end_bad, inv, lse);
+          store_piece_tile<RT, false>(a, O, r, inv, lse, 64 * g + 32 * r + n, dq, h, pid, end_b, whole);
+        }
+#pragma unroll
+        for (int T = 0; T < 4 * RT; ++T) O[T] = v16f{0};
+      }
+      if (unlikely(k == nblocks)) break;
       // B operand of row tile r: bytes 32h .. 32h+31 of row 32r + n (the K order
       // of the PV product, see the transposed reads)
       const int cs = (n >> 2) & 3;                  // chunk swizzle of rows n and 32 + n
@@ -553,6 +565,8 @@ __global__ __launch_bounds__(512, 1) void decode_stagger_kernel(DecodeArgs a, co
         P[r] = v8i{c0[0], c0[1], c0[2], c0[3], c1[0], c1[1], c1[2], c1[3]};
       }
       lds_wait_all();
+      // (at the end of the period, where this wave has time for the scalar loads)
+      if (k + 1 < nblocks && unlikely(gb + 1 >= cur.end)) seek(next, gb + 1);
     }
   }
 }

@@ -50,6 +50,9 @@ __device__ __forceinline__ void store_piece_tile(const DecodeArgs& a, const v16f
     uint16_t* dst = mine ? static_cast<uint16_t*>(a.out) + orow * kDc + 128 * dq + 4 * h
                          : reinterpret_cast<uint16_t*>(slot);
     const int bt = mine ? 32 : 2 * st, bq = mine ? 8 : 2 * sq;        // uint16 units
+    // (opaque, here and below: the products common to both branches would all be formed ahead of
+    // the branch, in 64 registers more)
+    asm volatile("" : "+v"(inv));
 #pragma unroll
     for (int T = 0; T < 4; ++T) {
 #pragma unroll
@@ -65,6 +68,7 @@ __device__ __forceinline__ void store_piece_tile(const DecodeArgs& a, const v16f
     // float32 rows (final or partial): four values (16 bytes) per store
     float* dst = mine ? static_cast<float*>(a.out) + orow * kDc + 128 * dq + 4 * h : slot;
     const int ft = mine ? 32 : st, fq = mine ? 8 : sq;
+    asm volatile("" : "+v"(inv));
 #pragma unroll
     for (int T = 0; T < 4; ++T) {
 #pragma unroll

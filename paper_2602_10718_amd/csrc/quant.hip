@@ -138,7 +138,6 @@ __global__ __launch_bounds__(256) void prep_kernel(PrepArgs a) {
       }
     }
     reinterpret_cast<uint32_t*>(a.zero)[tid] = 0u;   // 256 threads x 4 B = 1 KiB
-    if (tid == 0) a.ctrl[0] = a.out != nullptr ? 1 : 0;
     __syncthreads();                                 // prefix complete (LDS and global)
 
     // ---- start descriptors, one unit per thread ----------------------------
@@ -155,7 +154,11 @@ __global__ __launch_bounds__(256) void prep_kernel(PrepArgs a) {
     };
     // balanced plan over virtual positions (kPlanPad): sequence b spans [V_b, V_b+1),
     // V_b = prefix[b] + pad*b, its real blocks after its first pad positions
-    const int W = a.num_splits;
+    const int W = a.chunk_blocks == 0 ? plan_parts(a.num_splits, T + 2 * kPlanPad * a.B, a.plan_cost) : a.num_splits;
+    if (tid == 0) {
+      a.ctrl[0] = a.out != nullptr ? 1 : 0;
+      a.ctrl[1] = W;
+    }
     const int64_t TV = (int64_t)T + (int64_t)a.pad * a.B;
     auto vstart = [&](int b) { return (int64_t)pref(b) + (int64_t)a.pad * b; };
     auto real_in = [&](int b, int64_t v) {           // real blocks before v, v in b's span
@@ -178,7 +181,7 @@ __global__ __launch_bounds__(256) void prep_kernel(PrepArgs a) {
       int32_t* d = a.desc + (int64_t)u * kDescInts;
       int gs = 0, ge = 0, b = 0;
       if (a.chunk_blocks == 0) {
-        if (TV > 0) {
+        if (TV > 0 && u < W) {                       // (parts from W on stay empty)
           const int64_t vs = (int64_t)u * TV / W, ve = (int64_t)(u + 1) * TV / W;
           int bs, be;
           if (table) {

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stddef.h>
 #include <stdint.h>
 
@@ -24,6 +25,21 @@ WsLayout ws_layout(int B, int q_len, int H, int num_splits, int kv_chunk_tokens)
 // blocks' time with one row group).  With several row groups the period is the waves'
 // own work and equal block counts are kept (pad 0).
 constexpr int kPlanPad = 4;
+// Parts that a balanced plan uses of the num_splits it is given (plan_parts, on the device,
+// where the block count is known).  With W parts a workgroup's chain is T / W periods, while
+// every part writes, and the merge reads back, R rows of 2 KiB: T / W * period + W * R * 4 KiB /
+// bandwidth is least at W = sqrt(c T 64 / R), c = period * bandwidth / 256 KiB, about 28 for the
+// FP8 decode (1.4 us, 5 TB/s), twice that for the BF16 cache (two periods a block).  T counts
+// 2 kPlanPad blocks for every sequence: fewer parts hold more sequence boundaries each.
+// Measured, us per step (blocks, rows, sequences: best W and its time, all parts and their time):
+//   208, 128, 4: 64 30.1, 128 32.9;   451, 64, 8: 96 29.8, 256 33.3;   938, 64, 1: 128 36.1, 256 41.6
+//   1308, 64, 3: 192 36.1, 256 37.9;  898, 32, 8: 160 28.5, 256 30.5;  515, 64, 20: 160 29.4, 256 31.2
+//   285, 64, 79: 96 to 256 29.3 to 30.2;  2048, 128, 32 and 952, 16, 4 and 1963, 128, 116: all of them
+constexpr float kPlanCost = 28.0f;
+__host__ __device__ inline int plan_parts(int num_splits, int blocks, float cost) {
+  const int w = ((int)sqrtf(cost * (float)blocks) + 7) & ~7;   // (whole rounds of the eight XCDs)
+  return w < 8 ? (num_splits < 8 ? num_splits : 8) : (num_splits < w ? num_splits : w);
+}
 // units up to which the prep kernel maps units to sequences through an LDS table
 constexpr int kPlanTable = 1024;
 
@@ -39,10 +55,12 @@ struct PrepArgs {
   int32_t* desc;            // [units][kDescInts] start descriptor of each split unit (see kDesc*)
   int B, q_len, max_pages, chunk_blocks, num_splits, units;
   int pad = 0;              // balanced plan's virtual blocks per sequence start (WsLayout::pad)
+  float plan_cost = kPlanCost;   // c * 64 / R of plan_parts
   // Final results written by the decode itself (out != nullptr): the rows of sequences
   // without blocks (empty: o = 0, LSE = -inf; rejected by a data error: NaN), written by
   // the row waves, and ctrl[0] = 1, which tells the combine that the decode also wrote
-  // every sequence one piece covers (ctrl[0] = 0 when out is null: partials only).
+  // every sequence one piece covers (ctrl[0] = 0 when out is null: partials only);
+  // ctrl[1] = the parts of the balanced plan.
   int32_t* ctrl = nullptr;
   void* out = nullptr;              // [B*R][512] bf16 (out_dtype 0) or f32 (1)
   float* out_lse = nullptr;         // [B*R] or null
@@ -131,7 +149,8 @@ struct CombineArgs {
   const float* part_lse;
   const int32_t* prefix;
   const int32_t* flags;
-  const int32_t* ctrl;      // ctrl[0] == 1: sequences with at most one piece are final already
+  const int32_t* ctrl;      // ctrl[0] == 1: sequences with at most one piece are final already;
+                            // ctrl[1]: parts of the balanced plan
   const int32_t* seq_lens;
   void* out;
   float* lse;

@@ -52,3 +52,22 @@ def test_bad_page_marks_its_sequence_only(H, place):
     assert torch.isnan(run.out[1]).all() and torch.isnan(run.lse[1]).all()
     for b in (0, 2):
         assert torch.equal(run.out[b], good[0][b]) and torch.equal(run.lse[b], good[1][b])
+
+
+@pytest.mark.parametrize("H", [32, 64, 128])
+@pytest.mark.parametrize("B,n", [(1, 700), (3, 1500), (9, 130)])
+def test_fewer_parts_than_asked_for(H, B, n):
+    """Batches with few blocks use fewer parts than num_splits (the merge of a part costs as much as several blocks):
+    the same rows as with every sequence in one piece, up to the order of float32 sums (2^-16 of a row's largest
+    output: some 200 terms of at most that size, 2^-24 each)."""
+    lens = [n, n // 2 + 1, 0, 64][:B] + [n] * max(0, B - 4)
+    w = wl.custom(B=B, H=H, q_len=1, seq_lens=lens, seed=93, n_new=0)
+    one = runner(w, unsplit=True)
+    one.step()
+    for parts in (7, 8, 40, 1000):
+        run = runner(w, num_splits=parts, cache=(one.kv_latent, one.kv_scale, one.k_rope))
+        run.out.fill_(12345.0)
+        run.step()
+        torch.cuda.synchronize()
+        a, b = run.out.double().reshape(-1, 512), one.out.double().reshape(-1, 512)
+        assert ((a - b).abs().amax(1) <= 2.0 ** -16 * b.abs().amax(1)).all()
