@@ -2,6 +2,8 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 #include <stdint.h>
 
 namespace snapmla {
@@ -130,9 +132,17 @@ __device__ __forceinline__ float vmax16(const float (&v)[16]) {
   return vmax(vmax3(a, b, c), vmax3(d, e, v[15]));
 }
 
+// Maximum over the wave in every lane (whole wave active): lane permutations in registers
+// (a shuffle through LDS is six dependent round trips).
 __device__ __forceinline__ float wave_max(float x) {
-  for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
-  return x;
+  auto step = [&](auto ctrl) {
+    return fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), decltype(ctrl)::value, 0xF, 0xF, true)));
+  };
+  x = step(std::integral_constant<int, 0xB1>{});    // quad_perm [1,0,3,2]
+  x = step(std::integral_constant<int, 0x4E>{});    // quad_perm [2,3,0,1]
+  x = step(std::integral_constant<int, 0x141>{});   // row_half_mirror: the other quad of eight lanes
+  x = step(std::integral_constant<int, 0x140>{});   // row_mirror: the other eight of sixteen
+  return quad_max(x);
 }
 
 // s_waitcnt with only the vector-memory counter constrained (gfx9 encoding:
