@@ -15,6 +15,9 @@
 // 16-byte store), so every load instruction reads one 512-byte latent row and
 // every store writes one contiguous 1 KiB output span; the wave's 16 scales come
 // in one scalar load.  All loads of a wave are issued before the first convert.
+// Codes, RoPE and rows pass through the caches without staying (non-temporal): nothing of
+// them is read again by this kernel.  462 K tokens: 166.3 us without, 159.0 with the stores
+// alone, 162.3 with the loads alone, 156.1 (5.3 TB/s) with both.
 
 #include "snapmla_device.h"
 #include "snapmla_internal.h"
@@ -69,14 +72,15 @@ __global__ __launch_bounds__(256) void fetch_dequant_kernel(FetchArgs a) {
   // latent codes: 8 bytes of each of the wave's tokens (rows past the end are not read)
   v2i c[16];
 #pragma unroll
-  for (int t = 0; t < 16; ++t) c[t] = t < nt ? *reinterpret_cast<const v2i*>(lat + t * kDc) : v2i{0, 0};
+  for (int t = 0; t < 16; ++t) c[t] = t < nt ? __builtin_nontemporal_load(reinterpret_cast<const v2i*>(lat + t * kDc)) : v2i{0, 0};
   // RoPE: 16 tokens x 128 B = 2 KiB, 16 bytes per lane in two rounds (token 8i + lane/8, chunk lane%8)
   const uint8_t* rp = reinterpret_cast<const uint8_t*>(a.k_rope) + slot0 * (kDr * 2);
   v4i r[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int t = 8 * i + (lane >> 3);
-    r[i] = t < nt ? *reinterpret_cast<const v4i*>(rp + t * (kDr * 2) + 16 * (lane & 7)) : v4i{0, 0, 0, 0};
+    r[i] = t < nt ? __builtin_nontemporal_load(reinterpret_cast<const v4i*>(rp + t * (kDr * 2) + 16 * (lane & 7)))
+                  : v4i{0, 0, 0, 0};
   }
   float s[16];
 #pragma unroll
@@ -91,13 +95,13 @@ __global__ __launch_bounds__(256) void fetch_dequant_kernel(FetchArgs a) {
       const float st = s[t];
       const v4i o = v4i{(int)pack_bf16(f0[0] * st, f0[1] * st), (int)pack_bf16(f1[0] * st, f1[1] * st),
                         (int)pack_bf16(f2[0] * st, f2[1] * st), (int)pack_bf16(f3[0] * st, f3[1] * st)};
-      reinterpret_cast<v4i*>(out + t * kRowElems)[lane] = o;
+      __builtin_nontemporal_store(o, reinterpret_cast<v4i*>(out + t * kRowElems) + lane);
     }
   }
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int t = 8 * i + (lane >> 3);
-    if (t < nt) reinterpret_cast<v4i*>(out + t * kRowElems + kDc)[lane & 7] = r[i];
+    if (t < nt) __builtin_nontemporal_store(r[i], reinterpret_cast<v4i*>(out + t * kRowElems + kDc) + (lane & 7));
   }
 }
 
